@@ -167,34 +167,35 @@ static __device__ const double kExp2Table[32] = {
     0x1.ae89f995ad3adp+0, 0x1.b7f76f2fb5e47p+0, 0x1.c199bdd85529cp+0, 0x1.cb720dcef9069p+0,
     0x1.d5818dcfba487p+0, 0x1.dfc97337b9b5fp+0, 0x1.ea4afa2a490dap+0, 0x1.f50765b6e4540p+0};
 
-// exp of the covariance generation, e^{-r} for r >= 0.  FP64: with r clamped at
-// 700 (e^-700 is beyond the last bit of any covariance), k = rint(-32 r / ln 2)
+// exp of the covariance generation, e^{-r} for 0 <= r <= end; e^{-end} is 0, and the
+// callers clamp r there: the polynomials and squared differences that it multiplies
+// grow without limit, so that a smallest value other than 0 would not do (v_ldexp
+// instead of an addition to the exponent field: n = 1e6, m = 200 9.97 -> 10.07 ms,
+// the other paths within 1 %; a select on r > 708 cost the gradient paths 1-3 %).
+// Cody and Waite's reduction in both precisions.  FP64: k = rint(-32 r / ln 2)
 // from the low bits of a sum with 1.5 2^52, f = -r - k ln(2)/32 with ln(2)/32
 // split into a 34-bit leading part and the rest (|f| <= ln(2)/64), then e^f by its
 // Taylor series to degree 6 (truncation 4e-18) times 2^((k mod 32)/32) from a table
-// in LDS and 2^(k div 32) through the exponent field: the table's high words are
-// stored less i 2^15, so that adding k 2^15 to them does both.  Within one ulp
-// (mean 0.31); 13 FP64 and 4 integer instructions against 23 for the degree-13
-// series, and the 32 entries lie on 32 different bank pairs.
+// in LDS and 2^(k div 32) by v_ldexp, which underflows as the exact value does.
+// Within one ulp (mean 0.31) of normal results; the 32 entries lie on 32 different
+// bank pairs.
 // FP32: k = rint(-r / ln 2) the same way, v_exp_f32 of the rest (1/ln 2 in two
-// parts), exponent added; within the ulp of v_exp_f32.
+// parts) and 2^k by v_ldexp; within the ulp of v_exp_f32 for normal results (r < 87).
 template <typename T>
 struct ExpTable;
 template <>
 struct ExpTable<double> {
   static constexpr int n = 32;
-  __device__ static double entry(int i) {
-    return __hiloint2double(__double2hiint(kExp2Table[i]) - (i << 15), __double2loint(kExp2Table[i]));
-  }
+  static constexpr double end = 750.0;  // (e^-745.2 rounds to 0)
+  __device__ static double entry(int i) { return kExp2Table[i]; }
   // EXACT: within rounding; otherwise without the two highest terms of the series
   // (|f| <= ln 2 / 64: 2^-39)
   template <bool EXACT = true>
   __device__ __forceinline__ static double exp_neg(double r, const double* tab) {
-    const double x = -fmin(r, 700.0);
-    const double kd = fma(x, 0x1.71547652b82fep+5, 0x1.8p+52);
+    const double kd = fma(r, -0x1.71547652b82fep+5, 0x1.8p+52);
     const int k = __double2loint(kd);
     const double kf = kd - 0x1.8p+52;
-    double f = fma(-kf, 0x1.62e42fef80000p-6, x);
+    double f = fma(-kf, 0x1.62e42fef80000p-6, -r);
     f = fma(-kf, 0x1.1cf79abc9e3b4p-41, f);
     const double t = tab[k & 31];
     double q = 0x1.5555555555555p-5;
@@ -202,21 +203,21 @@ struct ExpTable<double> {
     q = fma(q, f, 0x1.5555555555555p-3);
     q = fma(q, f, 0.5);
     const double p = fma(f * f, q, f);
-    const double s = __hiloint2double(__double2hiint(t) + (k << 15), __double2loint(t));
+    const double s = __builtin_amdgcn_ldexp(t, k >> 5);
     return fma(s, p, s);
   }
 };
 template <>
 struct ExpTable<float> {
   static constexpr int n = 1;
+  static constexpr float end = 105.0f;  // (e^-104 rounds to 0)
   __device__ static float entry(int) { return 0.f; }
   __device__ __forceinline__ static float exp_neg(float r, const float*) {
-    const float x = -fminf(r, 87.0f);
-    const float kd = fmaf(x, 0x1.715476p+0f, 0x1.8p+23f);
+    const float kd = fmaf(r, -0x1.715476p+0f, 0x1.8p+23f);
     const float kf = kd - 0x1.8p+23f;
-    float f = fmaf(x, 0x1.715476p+0f, -kf);
-    f = fmaf(x, 0x1.4ae0c0p-26f, f);
-    return __int_as_float(__float_as_int(__builtin_amdgcn_exp2f(f)) + (__float_as_int(kd) << 23));
+    float f = fmaf(r, -0x1.715476p+0f, -kf);
+    f = fmaf(r, -0x1.4ae0c0p-26f, f);
+    return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), __float_as_int(kd) - __float_as_int(0x1.8p+23f));
   }
 };
 

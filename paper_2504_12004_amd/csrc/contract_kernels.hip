@@ -116,7 +116,7 @@ __device__ __forceinline__ void contract_rows(const typename ZV<T>::v* zs, const
                 r2 += ds[kOV<T> * e + u];
               }
             }
-            const T r = c_sqrt(r2), ex = ExpTable<T>::exp_neg(r, tab);
+            const T r = fmin(c_sqrt(r2), ExpTable<T>::end), ex = ExpTable<T>::exp_neg(r, tab);
             const T M = fma(ea, gb, fma(ga, sb, -P[t]));
             const T rho = fma(r, fma(r, fma(r, cov.p3, cov.p2), cov.p1), cov.p0) * ex;
             T h = fma(r, fma(r, cov.h2, cov.h1), cov.h0) * ex;

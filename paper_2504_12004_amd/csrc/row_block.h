@@ -299,8 +299,9 @@ struct Cov {
   }
   template <bool EXACT>
   __device__ __forceinline__ double eval(double r2, const double* tab) const {
-    const double r = c_sqrt<EXACT>(r2);
-    return fma(r, fma(r, fma(r, p3, p2), p1), p0) * ExpTable<double>::exp_neg<EXACT>(r, tab);
+    const double r = c_sqrt<EXACT>(r2);  // (NaN where r2 overflows: it has to reach the pivots)
+    return fma(r, fma(r, fma(r, p3, p2), p1), p0) *
+           ExpTable<double>::exp_neg<EXACT>(fmin(r, ExpTable<double>::end), tab);
   }
 };
 

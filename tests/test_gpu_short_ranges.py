@@ -1,0 +1,55 @@
+"""Value and gradient where every pair of points is many ranges apart: the
+covariance is sigma^2 e^{-r} times a polynomial in r, 0 beyond r = 745 in FP64 and
+104 in FP32, and stays 0 however large the polynomial and the squared differences
+of the derivatives become (a line search may step to such ranges: theta only has to
+be finite).
+
+Against the FP64 oracle, at scaled distances of the given order.  FP64: 1e-10 of
+the value and 1e-8 max(|g|_inf, 1) per component, as elsewhere.  FP32: the backward
+error of the factorisation and of the two solves, 2 n_A 2^-24 (sigma^2 + tau^2) /
+tau^2, of terms of order one per own point, summed over the blocks (sigma^2 =
+tau^2 = 1).
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+from helpers import to_gpu
+from paper_2504_12004_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sbv():
+    from paper_2504_12004_amd import sbv as S
+    return S
+
+
+def _check(sbv, dist, two_nu, prec):
+    n, d = 120, 3
+    X, _, _ = synth.random_spd_problem(n, d, 5)
+    y = np.random.default_rng(6).standard_normal(n)
+    S = O.build(X, np.ones(d), K=8, m=40, lloyd_iters=2, seed=1)
+    # distances between the points are between about 0.05 and 1.5
+    th = np.r_[-np.log(dist) + np.array([0.1, 0.0, -0.1]), 0.0, 0.0]
+    ref_l, ref_g = O.sbv_loglik(X, y, S, th, two_nu, grad=True)
+    assert np.isfinite(ref_l) and np.all(np.isfinite(ref_g))
+    B = to_gpu(sbv, X, y, S)
+    l, g = sbv.sbv_loglik_grad(B, th, two_nu, prec)
+    v = sbv.sbv_loglik(B, th, two_nu, prec)
+    B.free()
+    own, joint = np.diff(S.block_ptr), np.diff(S.nn_ptr) + np.diff(S.block_ptr)
+    bar32 = 2 * 2.0 ** -24 * 2 * np.sum(own * joint)
+    bar_l, bar_g = (bar32, bar32) if prec else (1e-10 * abs(ref_l), 1e-8 * max(1.0, np.max(np.abs(ref_g))))
+    print(f"l {l[0] - ref_l:.2e} v {v[0] - ref_l:.2e} of {bar_l:.2e}; g {np.max(np.abs(g - ref_g)):.2e} of {bar_g:.2e}",
+          flush=True)
+    assert abs(l[0] - ref_l) <= bar_l and abs(v[0] - ref_l) <= bar_l
+    assert np.max(np.abs(g - ref_g)) <= bar_g
+
+
+@pytest.mark.parametrize("prec,dist", [(0, 80.0), (0, 700.0), (0, 1e3), (0, 1e9), (0, 1e78), (0, 1e95),
+                                       (1, 80.0), (1, 90.0), (1, 1e3), (1, 1e9), (1, 1e12), (1, 1e14)])
+@pytest.mark.parametrize("two_nu", [1, 3, 5, 7])
+def test_distant_points(sbv, two_nu, prec, dist):
+    _check(sbv, dist, two_nu, prec)
