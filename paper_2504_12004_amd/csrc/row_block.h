@@ -668,8 +668,11 @@ __global__ __launch_bounds__(NW * 64, OCC) void k_block_rows(const SetDesc* __re
     const T diag0 = T(sigma2) + T(tau2), tau = T(piv_tau);
     const Cov cov(sigma2, S.two_nu);
 
+    bool bad = false, low = false;
     // gather A = J u B (J first), one point per thread, twelve coordinates in
-    // flight at once; padding points are zero
+    // flight at once; padding points are zero.  The contraction works with FP32
+    // coordinates in the FP32 path: a block whose squared differences could leave
+    // their range (20 (2 10^18)^2 < 2^128) goes to the FP64 pass with both kernels.
     for (int pl = tid; pl < nt * kTile; pl += NW * 64) {
       const bool real = pl < nA;
       const int pos = !real ? b0 : pl < mi ? as_global(S.nidx)[n0 + pl] : b0 + (pl - mi);
@@ -687,6 +690,10 @@ __global__ __launch_bounds__(NW * 64, OCC) void k_block_rows(const SetDesc* __re
 #pragma unroll
           for (int u = 0; u < kOV<double>; ++u)
             v[u] = (real && e0 + i + u < d) ? x[i + u] * sm.isc[min(e0 + i + u, d - 1)] : 0.0;
+          if constexpr (ADJ && sizeof(T) == 4) {
+#pragma unroll
+            for (int u = 0; u < kOV<double>; ++u) low |= !(fabs(v[u]) <= 1e18);
+          }
           reinterpret_cast<typename ZV<double>::v*>(z)[NTM * kTile * ((e0 + i) / kOV<double>) + pl] = v;
         }
       }
@@ -708,7 +715,6 @@ __global__ __launch_bounds__(NW * 64, OCC) void k_block_rows(const SetDesc* __re
     for (int i = 0; i < NR; ++i) R[i] = acc_t{T(0), T(0), T(0), T(0)};
 #pragma unroll
     for (int s = 0; s < NS; ++s) part[s] = vpart[s] = T(0);
-    bool bad = false, low = false;
     __syncthreads();
     if constexpr (CAP > 0) {  // diagonal tiles
       const int lane = tid & 63;

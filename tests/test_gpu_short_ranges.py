@@ -53,3 +53,10 @@ def _check(sbv, dist, two_nu, prec):
 @pytest.mark.parametrize("two_nu", [1, 3, 5, 7])
 def test_distant_points(sbv, two_nu, prec, dist):
     _check(sbv, dist, two_nu, prec)
+
+
+@pytest.mark.parametrize("dist", [1e17, 1e19, 1e20, 1e40, 1e95])
+@pytest.mark.parametrize("two_nu", [1, 3, 5, 7])
+def test_distances_beyond_fp32(sbv, two_nu, dist):
+    # squared differences and coordinates that FP32 cannot hold: blocks are redone in FP64
+    _check(sbv, dist, two_nu, 1)
