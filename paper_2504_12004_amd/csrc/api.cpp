@@ -341,12 +341,15 @@ std::vector<TimedLaunch> g_timed;
 #define g_piv_tau sbv::fp32_pivot_tau()
 
 // Allocate the per-block adjoint buffers (e, g, Q: nA_i (b_i + 2) values per
-// block) of every set of a plan, once.
+// block) of every set of a plan, once.  The plan takes them when all are there: a
+// call that ran out of memory leaves it as it was, and the next one starts again.
 sbv_status ensure_adjoint(Plan* P) {
   if (!P->qbuf.empty()) return SBV_OK;
   const int ns = (int)P->sets.size();
-  P->qbuf.resize(ns);
-  P->qoff.resize(ns);
+  std::vector<DevBuf<double>> qbuf(ns);
+  std::vector<DevBuf<int64_t>> qoff(ns);
+  DevBuf<double> grad, adj_tiles;
+  std::vector<SetDesc> hd = P->hdesc;
   for (int s = 0; s < ns; ++s) {
     sbv_blocks h = P->sets[s];
     std::vector<int64_t> off(h->K + 1, 0);
@@ -354,14 +357,13 @@ sbv_status ensure_adjoint(Plan* P) {
       const int64_t bi = h->block_ptr[b + 1] - h->block_ptr[b];
       off[b + 1] = off[b] + (int64_t)h->joint[b] * (bi + 2);
     }
-    HIP_TRY(P->qbuf[s].alloc(off[h->K]));
-    HIP_TRY(P->qoff[s].alloc(h->K + 1));
-    HIP_TRY(hipMemcpy(P->qoff[s].p, off.data(), sizeof(int64_t) * (h->K + 1), hipMemcpyHostToDevice));
-    P->hdesc[s].qbuf = P->qbuf[s].p;
-    P->hdesc[s].qoff = P->qoff[s].p;
+    HIP_TRY(qbuf[s].alloc(off[h->K]));
+    HIP_TRY(qoff[s].alloc(h->K + 1));
+    HIP_TRY(hipMemcpy(qoff[s].p, off.data(), sizeof(int64_t) * (h->K + 1), hipMemcpyHostToDevice));
+    hd[s].qbuf = qbuf[s].p;
+    hd[s].qoff = qoff[s].p;
   }
-  HIP_TRY(hipMemcpy(P->dsets.p, P->hdesc.data(), sizeof(SetDesc) * ns, hipMemcpyHostToDevice));
-  HIP_TRY(P->grad.alloc(P->theta_len));
+  HIP_TRY(grad.alloc(P->theta_len));
   size_t elems = 0;  // (FP64 elements; the buckets run one after the other)
   for (auto& B : P->buckets) {
     if (B.large) continue;
@@ -370,7 +372,13 @@ sbv_status ensure_adjoint(Plan* P) {
       elems = std::max(elems, p ? (e + 1) / 2 : e);
     }
   }
-  if (elems) HIP_TRY(P->adj_tiles.alloc(elems));
+  if (elems) HIP_TRY(adj_tiles.alloc(elems));
+  HIP_TRY(hipMemcpy(P->dsets.p, hd.data(), sizeof(SetDesc) * ns, hipMemcpyHostToDevice));
+  P->hdesc.swap(hd);
+  P->grad = std::move(grad);
+  P->adj_tiles = std::move(adj_tiles);
+  P->qoff.swap(qoff);
+  P->qbuf.swap(qbuf);
   return SBV_OK;
 }
 

@@ -1,0 +1,124 @@
+"""Device memory of the evaluation plans, on the CPU: a stand-in for the HIP runtime's
+memory and launch calls (host memory, launches that do nothing) counts what the
+library allocates and refuses what a test asks it to.  Each scenario runs in a
+process of its own, in which the stand-in is loaded before the library."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+STUB = r"""
+#include <stdlib.h>
+#include <string.h>
+typedef struct { unsigned x, y, z; } dim3_t;
+long live = 0, calls = 0, launches = 0, fail_at = 0, max_bytes = -1;
+int capturing = 0;
+int hipMalloc(void** p, size_t n) {
+  ++calls;
+  *p = NULL;
+  if (calls == fail_at || (max_bytes >= 0 && (long)n > max_bytes)) return 2; /* out of memory */
+  char* b = calloc(1, n + 64);
+  if (!b) return 2;
+  *(size_t*)b = n;
+  live += n;
+  *p = b + 64;
+  return 0;
+}
+int hipFree(void* p) {
+  if (!p) return 0;
+  live -= *(size_t*)((char*)p - 64);
+  free((char*)p - 64);
+  return 0;
+}
+int hipMemcpy(void* d, const void* s, size_t n, int k) { memcpy(d, s, n); return 0; }
+int hipMemcpyAsync(void* d, const void* s, size_t n, int k, void* st) { memcpy(d, s, n); return 0; }
+int __hipPushCallConfiguration(dim3_t g, dim3_t b, size_t l, void* s) { return 0; }
+int __hipPopCallConfiguration(dim3_t* g, dim3_t* b, size_t* l, void** s) {
+  *g = *b = (dim3_t){1, 1, 1};
+  *l = 0;
+  *s = NULL;
+  return 0;
+}
+int hipLaunchKernel(const void* f, dim3_t g, dim3_t b, void** a, size_t l, void* s) { ++launches; return 0; }
+int hipGetLastError(void) { return 0; }
+int hipGetDeviceCount(int* n) { *n = 1; return 0; }
+int hipGetDevice(int* d) { *d = 0; return 0; }
+int hipMemset(void* d, int v, size_t n) { memset(d, v, n); return 0; }
+int hipDeviceSynchronize(void) { return 0; }
+int hipStreamIsCapturing(void* s, int* st) { *st = capturing; return 0; }
+"""
+
+PRELUDE = """
+import ctypes, sys
+import numpy as np
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+var = lambda n: ctypes.c_long.in_dll(stub, n)
+from paper_2504_12004_amd import sbv
+
+def handle(joint, count, own=1):
+    # `count` blocks of `own` points each on the `joint - own` points before them
+    lead = joint - own
+    sizes = [1] * lead + [own] * count
+    bp = np.r_[0, np.cumsum(sizes)]
+    n = int(bp[-1])
+    idx = [np.arange(bp[r] - (lead if r >= lead else 0), bp[r]) for r in range(len(sizes))]
+    X = np.random.default_rng(0).random((n, 2))
+    return sbv.sbv_blocks_import(X, np.zeros(n), bp, np.arange(n), np.r_[0, np.cumsum([len(i) for i in idx])],
+                                 np.concatenate(idx))
+
+theta = np.zeros(4)
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    d = tmp_path_factory.mktemp("stub")
+    (d / "stub.c").write_text(STUB)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", str(d / "stub.so"), str(d / "stub.c")], check=True)
+    return str(d / "stub.so")
+
+
+def _run(stub, body):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), stub], cwd=ROOT, capture_output=True,
+                       text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_gradient_after_running_out_of_memory(stub):
+    """Whichever allocation of the first gradient call fails, the next call has the
+    buffers that an undisturbed one has."""
+    _run(stub, """
+    def grad(h, fail):
+        before = var("calls").value
+        var("fail_at").value = before + fail if fail else 0
+        st = sbv.SBV_OK
+        try:
+            sbv.sbv_loglik_grad(h, theta, 5)
+        except sbv.SBVError as e:
+            st = e.status
+        var("fail_at").value = 0
+        return st, var("calls").value - before
+
+    def fresh():
+        h = handle(100, 20)
+        sbv.sbv_loglik(h, theta, 5, sbv.SBV_FP32)  # the plan
+        return h
+
+    h = fresh()
+    st, count = grad(h, 0)
+    whole = var("live").value
+    assert st == 0 and count >= 4, (st, count)
+    h.free()
+    for i in range(1, count + 1):
+        h = fresh()
+        assert grad(h, i)[0] == sbv.SBV_E_NOMEM
+        assert grad(h, 0)[0] == 0
+        assert var("live").value == whole, (i, var("live").value, whole)
+        assert grad(h, 0) == (0, 0)
+        h.free()
+    assert var("live").value == 0
+    """)
