@@ -122,3 +122,49 @@ def test_gradient_after_running_out_of_memory(stub):
         h.free()
     assert var("live").value == 0
     """)
+
+
+def test_memory_for_the_factor_is_made_by_fp64_values(stub):
+    """Blocks of 13 to 17 tiles keep a part of the factor in memory in FP64 values:
+    FP32 values and gradients do not allocate it, a captured call and one that finds
+    no memory do without it, and a gradient's buffers do not come with it."""
+    _run(stub, """
+    slots = 512 * 256 * 8  # workgroups, elements of a tile
+
+    class Ptr:
+        def __init__(self, a):
+            self.a = a
+        def data_ptr(self):
+            return self.a.ctypes.data
+
+    th, out = Ptr(theta), Ptr(np.zeros(1))
+    for joint, ntm in ((200, 14), (250, 16), (272, 17)):
+        tiles = slots * ntm * (ntm + 1) // 2
+        h = handle(joint, 600)
+        base = var("live").value
+        sbv.sbv_loglik(h, theta, 5, sbv.SBV_FP32)
+        assert var("live").value - base < 1 << 20
+        calls = var("calls").value
+        var("capturing").value = 1
+        sbv.sbv_loglik_dev(h, th, 5, out, stream=1)
+        var("capturing").value = 0
+        assert var("calls").value == calls
+        sbv.sbv_loglik_dev(h, th, 5, out, stream=1)
+        assert tiles <= var("live").value - base < tiles + (1 << 20), (joint, var("live").value - base, tiles)
+        calls = var("calls").value
+        sbv.sbv_loglik(h, theta, 5)
+        sbv.sbv_loglik(h, theta, 5, sbv.SBV_FP32)
+        assert var("calls").value == calls
+        h.free()
+
+        h = handle(joint, 600)
+        launches = var("launches").value
+        var("max_bytes").value = 1 << 24
+        sbv.sbv_loglik(h, theta, 5)
+        refused = var("calls").value
+        sbv.sbv_loglik(h, theta, 5)
+        assert var("calls").value == refused and var("launches").value > launches
+        var("max_bytes").value = -1
+        h.free()
+    assert var("live").value == 0
+    """)
