@@ -814,6 +814,10 @@ static sbv_status ensure_sampler(sbv_blocks h, int32_t two_nu) {
       merge_small(per);
       for (int v = 0; v < nv; ++v) per[v].swap(lists[(size_t)l * nv + v]);
     }
+    // (the handle takes the buffers when all are there)
+    std::vector<sbv_blocks_s::SampleLevel> levels;
+    DevBuf<double> xi_ord, theta_s;
+    DevBuf<SetDesc> desc;
     for (size_t li = 0; li < lists.size(); ++li) {
       if (lists[li].empty()) continue;
       sbv_blocks_s::SampleLevel L;
@@ -823,11 +827,15 @@ static sbv_status ensure_sampler(sbv_blocks h, int32_t two_nu) {
       HIP_TRY(hipMemcpy(L.items.p, lists[li].data(), sizeof(WorkItem) * L.count, hipMemcpyHostToDevice));
       HIP_TRY(L.dcount.alloc(1));
       HIP_TRY(hipMemcpy(L.dcount.p, &L.count, sizeof(int), hipMemcpyHostToDevice));
-      h->sample_levels.push_back(std::move(L));
+      levels.push_back(std::move(L));
     }
-    HIP_TRY(h->xi_ord.alloc(h->n));
-    HIP_TRY(h->theta_s.alloc(h->d + 2));
-    HIP_TRY(h->sample_desc.alloc(1));
+    HIP_TRY(xi_ord.alloc(h->n));
+    HIP_TRY(theta_s.alloc(h->d + 2));
+    HIP_TRY(desc.alloc(1));
+    h->sample_levels.swap(levels);
+    h->xi_ord = std::move(xi_ord);
+    h->theta_s = std::move(theta_s);
+    h->sample_desc = std::move(desc);
   }
   SetDesc D{};
   D.X = h->X.p;

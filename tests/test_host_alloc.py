@@ -124,6 +124,35 @@ def test_gradient_after_running_out_of_memory(stub):
     """)
 
 
+def test_simulation_after_running_out_of_memory(stub):
+    """Likewise the first simulation's work lists and buffers."""
+    _run(stub, """
+    def sample(h, fail):
+        before = var("calls").value
+        var("fail_at").value = before + fail if fail else 0
+        st = sbv.SBV_OK
+        try:
+            sbv.sbv_sample(h, theta, 5, np.zeros(119))
+        except sbv.SBVError as e:
+            st = e.status
+        var("fail_at").value = 0
+        return st, var("calls").value - before
+
+    h = handle(100, 20)
+    st, count = sample(h, 0)
+    whole = var("live").value
+    assert st == 0 and count >= 8, (st, count)
+    h.free()
+    for i in range(1, count + 1):
+        h = handle(100, 20)
+        assert sample(h, i)[0] == sbv.SBV_E_NOMEM
+        assert sample(h, 0)[0] == 0
+        assert var("live").value == whole, (i, var("live").value, whole)
+        h.free()
+    assert var("live").value == 0
+    """)
+
+
 def test_memory_for_the_factor_is_made_by_fp64_values(stub):
     """Blocks of 13 to 17 tiles keep a part of the factor in memory in FP64 values:
     FP32 values and gradients do not allocate it, a captured call and one that finds
