@@ -26,7 +26,10 @@
  *    the stream reaches that point.
  *  - Errors: every function returns an sbv_status; on failure outputs are left
  *    untouched unless stated, and sbv_last_error() describes the failure.
- *  - One handle must not be used from two host threads at once.
+ *  - One handle must not be used from two host threads at once.  Evaluations
+ *    queued on several streams share a handle's block terms and flags and, for
+ *    the same list of handles, parameters, outputs and the memory of a part of
+ *    the factor: order them.
  */
 #ifndef SBV_H
 #define SBV_H
@@ -135,7 +138,7 @@ sbv_status sbv_loglik_dev(const sbv_blocks* sets, int32_t n_sets, const double* 
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * log-likelihood of ONE handle, as sbv_loglik_dev computes it (same kernels,
  * size buckets and reduction with the default kernel choice, so the same value
- * bit for bit unless sbv_autotune changed that choice), queued on `stream` (a hipStream_t; NULL = default stream) with no
+ * bit for bit), queued on `stream` (a hipStream_t; NULL = default stream) with no
  * allocation and no host synchronisation.  theta_dev (d+2 log-parameters) and
  * loglik_dev (1 value, -inf when a block is not positive definite) are device
  * pointers owned by the caller.  The per-block terms, flags, FP32 fallback
@@ -337,8 +340,9 @@ sbv_status sbv_eval_graph_dev(const sbv_blocks* sets, int32_t n_sets, const doub
  * entries) the waves per compute unit of the chosen kernel (waves per workgroup
  * times the workgroups it is built to share a unit with).  Then whole
  * evaluations with one launch per size bucket are timed against ONE persistent
- * launch for all blocks of all sets with joint sizes up to 272 (the largest chosen variant, workgroups taking blocks longest first
- * from a device counter); chosen_persistent (optional) receives 1 when the
+ * launch for all blocks of all sets with joint sizes up to 272 (the largest
+ * chosen variant, workgroups taking blocks longest first from a device
+ * counter); chosen_persistent (optional) receives 1 when the
  * persistent launch won.  The environment variable SBV_PERSISTENT=1 / =0
  * overrides that choice at evaluation time.  Synchronous.
  */

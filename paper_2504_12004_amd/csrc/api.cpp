@@ -411,8 +411,8 @@ sbv_status run_plan_grad(Plan* P, int32_t prec, hipStream_t s) {
     auto adjoint = [&](int prec_k, int grid, const WorkItem* items, const int* count, double tau) -> hipError_t {
       hipError_t e;
       if (B.large)
-        e = launch_large(prec_k, true, B.max_joint, std::min(B.slots[prec_k], large_slots(prec_k, true)), P->dmax, P->dsets.p, P->theta.p, items, count,
-                         tau, B.tiles.p, s);
+        e = launch_large(prec_k, true, B.max_joint, std::min(B.slots[prec_k], large_slots(prec_k, true)), P->dmax,
+                         P->dsets.p, P->theta.p, items, count, tau, B.tiles.p, s);
       else
         e = launch_loglik_adjoint(prec_k, B.variant, std::min(B.count, adjoint_slots(prec_k, B.variant)), P->dmax,
                                   P->dsets.p, P->theta.p, items, count, tau, P->adj_tiles.p, s);
@@ -422,11 +422,11 @@ sbv_status run_plan_grad(Plan* P, int32_t prec, hipStream_t s) {
     if (pk) {
       HIP_TRY(launch_zero_int(B.fb_count.p, 1, s));
       HIP_TRY(launch_flag_compact(P->dsets.p, B.items.p, B.dcount.p, B.fb_items.p, B.fb_count.p, s));
-      const int grid = std::min(B.count, max_grid(0, B.large ? n_variants() - 1 : B.variant));
+      const int grid = std::min(B.count, max_grid(B.large ? n_variants() - 1 : B.variant));
       HIP_TRY(adjoint(0, grid, B.fb_items.p, B.fb_count.p, 0.0));
     }
   }
-  HIP_TRY(launch_reduce(P->dsets.p, (int)P->sets.size(), nullptr, P->out.p, P->bad.p, s));
+  HIP_TRY(launch_reduce(P->dsets.p, (int)P->sets.size(), P->out.p, P->bad.p, s));
   HIP_TRY(launch_reduce_grad(P->dsets.p, (int)P->sets.size(), P->dmax, P->grad.p, P->bad.p, s));
   return SBV_OK;
 }
@@ -513,14 +513,14 @@ sbv_status run_plan(Plan* P, int32_t prec, hipStream_t s, int force_persistent =
         HIP_TRY(launch_large(0, false, B.max_joint, B.slots[0], P->dmax, P->dsets.p, P->theta.p, B.fb_items.p,
                              B.fb_count.p, 0.0, B.tiles.p, s));
       } else {
-        int grid = std::min(B.count, max_grid(0, B.use(0)));
+        int grid = std::min(B.count, max_grid(B.use(0)));
         double* const tiles = B.tiles_for(0, B.use(0), &grid);
         HIP_TRY(launch_loglik(0, B.use(0), grid, P->dmax, P->dsets.p, P->theta.p, B.fb_items.p, B.fb_count.p, 0.0, s,
                               nullptr, tiles));
       }
     }
   }
-  HIP_TRY(launch_reduce(P->dsets.p, (int)P->sets.size(), nullptr, P->out.p, P->bad.p, s));
+  HIP_TRY(launch_reduce(P->dsets.p, (int)P->sets.size(), P->out.p, P->bad.p, s));
   return SBV_OK;
 }
 

@@ -35,14 +35,13 @@ struct MF<float> {
   __device__ static constexpr int row(int g, int t) { return 4 * g + t; }
 };
 
-// e^x for the covariance generation (x = -r <= 0): Cody and Waite's reduction
+// e^x of the dense covariance matrix (x = -r <= 0): Cody and Waite's reduction
 // x = k ln 2 + f, k = rint(x / ln 2), |f| <= ln(2) / 2, with ln 2 split into a
 // 42-bit leading part (k ln2_hi is exact for |k| < 2^11) and the rest; then
 // e^f = 1 + (f + f^2 P(f)), P the Taylor series of (e^f - 1 - f) / f^2 to
 // degree 11 (truncation below 1e-17 relative), evaluated by Estrin's scheme:
-// the dependent chain is 6 operations deep against Horner's 13 (the
-// generation is latency-bound), and adding the 1 last keeps the error within
-// one ulp; finally scaled by 2^k.  x is clamped at -1000, where e^x is 0.
+// the dependent chain is 6 operations deep against Horner's 13, and adding the 1
+// last keeps the error within one ulp; finally scaled by 2^k.  x is clamped at -1000, where e^x is 0.
 __device__ __forceinline__ double t_exp(double x) {
   x = fmax(x, -1000.0);
   const double k = rint(x * 0x1.71547652b82fep+0);
@@ -59,7 +58,7 @@ __device__ __forceinline__ double t_exp(double x) {
   const double p = fma(e2, f8, fma(e1, f4, e0));
   return __builtin_amdgcn_ldexp(1.0 + fma(f2, p, f), (int)k);
 }
-// Distance from its square in the covariance generation (r2 >= 0): the
+// Distance from its square in the dense covariance matrix (r2 >= 0): the
 // hardware reciprocal square root (about 23 good bits) refined by one coupled
 // Newton-Raphson step for sqrt(r2) and 1/(2 sqrt(r2)) and one residual
 // correction (Goldschmidt's square-root iteration as in Markstein's IA-64
@@ -93,8 +92,7 @@ struct ZV<float> {
 // Matern correlation, closed forms of Eq. (maternkernel) for half-integer nu:
 // p(r) e^{-r} with p = 1, 1 + r, 1 + r + r^2/3, 1 + r + 2 r^2/5 + r^3/15 for
 // nu = 1/2, 3/2, 5/2, 7/2, taken as 1 + r (c1 + r (c2 + r c3)) with the
-// coefficients selected once from the (uniform) smoothness: no branch per
-// entry, so that the covariance generation can interleave its entries.
+// coefficients selected once from the (uniform) smoothness (dense covariance matrix).
 template <typename T>
 __device__ __forceinline__ T matern(T r, int two_nu) {
   const T c1 = two_nu >= 3 ? T(1) : T(0);

@@ -7,10 +7,9 @@
 
 namespace sbv {
 
-int max_grid(int prec, int v) {
-  (void)prec;
-  // enough resident workgroups to fill 256 CUs several times over
-  return 256 * 8 / (variant(v).ntm > 8 ? 4 : 1);
+int max_grid(int v) {
+  // enough workgroups to fill the chip several times over
+  return kUnits * 8 / (variant(v).ntm > 8 ? 4 : 1);
 }
 
 // ---- deterministic per-set reduction of the block terms ------------------
@@ -47,9 +46,7 @@ __global__ __launch_bounds__(kRed) void k_reduce(const SetDesc* __restrict__ set
   }
 }
 
-hipError_t launch_reduce(const SetDesc* sets, int n_sets, const int* set_k, double* out, int* bad,
-                         hipStream_t s) {
-  (void)set_k;
+hipError_t launch_reduce(const SetDesc* sets, int n_sets, double* out, int* bad, hipStream_t s) {
   hipLaunchKernelGGL(k_reduce, dim3(n_sets), dim3(kRed), 0, s, sets, out, bad);
   return hipGetLastError();
 }

@@ -138,10 +138,10 @@ extern "C" sbv_status sbv_loglik_noalloc_dev(sbv_blocks h, const double* theta_d
     if (pk) {
       NA_TRY(sbv::launch_zero_int(fb_count + b, 1, s));
       NA_TRY(sbv::launch_flag_compact(desc, items, v.dcount + b, fb_items, fb_count + b, s));
-      const int grid = std::min(v.bucket_count[b], sbv::max_grid(0, var));
+      const int grid = std::min(v.bucket_count[b], sbv::max_grid(var));
       NA_TRY(sbv::launch_loglik(0, var, grid, v.d, desc, theta_dev, fb_items, fb_count + b, 0.0, s));
     }
   }
-  NA_TRY(sbv::launch_reduce(desc, 1, nullptr, loglik_dev, bad, s));
+  NA_TRY(sbv::launch_reduce(desc, 1, loglik_dev, bad, s));
   return SBV_OK;
 }

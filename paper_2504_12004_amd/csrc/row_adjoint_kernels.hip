@@ -3,7 +3,7 @@
 
 namespace sbv {
 
-int adjoint_slots(int prec, int v) { return 256 * (4 * (prec == 0 ? kRow[v].occ64 : kRow[v].adj32) / kRow[v].nw); }
+int adjoint_slots(int prec, int v) { return kUnits * (4 * (prec == 0 ? kRow[v].occ64 : kRow[v].adj32) / kRow[v].nw); }
 
 hipError_t launch_loglik_adjoint(int prec, int v, int grid, int dmax, const SetDesc* sets, const double* theta,
                                  const WorkItem* items, const int* count, double piv_tau, void* tiles, hipStream_t s) {

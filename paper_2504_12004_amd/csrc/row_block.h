@@ -308,13 +308,13 @@ struct Cov {
 // Negated covariance tiles (row[n], k), n < N, in the accumulator layout of the
 // transposed tile: register t of lane (g, c) is the entry of points 16 k + g +
 // 4t and 16 row[n] + c.  Coordinates (FP64) are stored as 16-byte vectors of two
-// dimensions, P points per vector row, so that every read has a constant offset;
-// the next vector is read while the current one is used.  The four points of tile
-// k are read once for all N rows.  Only the last tile row and column (padding:
-// identity) and diagonal tiles (nugget) need their entries looked at.
+// dimensions, P points per vector row, so that every read has a constant offset
+// (reading the next vector while one is used spills: 8325 against 8060 us, 14 tiles).
+// The four points of tile k are read once for all N rows.  Only the last tile row and
+// column (padding: identity) and diagonal tiles (nugget) need their entries looked at.
 // NAT: rows in the MFMA output's own order (diagonal tiles, whose A operand is
 // the unpermuted register).
-template <typename T, int N, int P, bool NAT = false, bool PF = false>
+template <typename T, int N, int P, bool NAT = false>
 __device__ __forceinline__ void gen_tiles(const double* z, const double* tab, int nv, int lane, int k, const int (&row)[N],
                                           int nt, int nA, const Cov& cov, double tau2, double (&v)[N][4]) {
   typedef typename ZV<double>::v zv;
@@ -322,12 +322,12 @@ __device__ __forceinline__ void gen_tiles(const double* z, const double* tab, in
   auto prow = [](int g, int t) { return NAT ? MF<T>::row(g, t) : g + 4 * t; };
   const zv* za = reinterpret_cast<const zv*>(z) + kTile * k + prow(g, 0);
   const zv* zb[N];
-  zv a[PF ? 2 : 1][4], b[PF ? 2 : 1][N];
-  auto load = [&](int e, int h) {
+  zv a[4], b[N];
+  auto load = [&]() {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) a[h][t] = za[P * e + prow(0, t)];
+    for (int t = 0; t < 4; ++t) a[t] = za[prow(0, t)];
 #pragma unroll
-    for (int n = 0; n < N; ++n) b[h][n] = zb[n][P * e];
+    for (int n = 0; n < N; ++n) b[n] = zb[n][0];
   };
 #pragma unroll
   for (int n = 0; n < N; ++n) {
@@ -335,39 +335,23 @@ __device__ __forceinline__ void gen_tiles(const double* z, const double* tab, in
 #pragma unroll
     for (int t = 0; t < 4; ++t) v[n][t] = kTinyR2<double>;
   }
-  auto add = [&](int h) {
+  auto add = [&]() {
 #pragma unroll
     for (int n = 0; n < N; ++n)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const zv df = a[h][t] - b[h][n];
+        const zv df = a[t] - b[n];
 #pragma unroll
         for (int x = 0; x < kOV<double>; ++x) v[n][t] += df[x] * df[x];
       }
   };
-  if constexpr (PF) {
-    load(0, 0);
 #pragma unroll 1
-    for (int e = 1; e <= nv; e += 2) {
-      if (e < nv) load(1, 1);
-      add(0);
-      if (e < nv) {
-        if (e + 1 < nv) load(2, 0);
-        add(1);
-      }
-      za += 2 * P;
+  for (int e = 0; e < nv; ++e) {
+    load();
+    add();
+    za += P;
 #pragma unroll
-      for (int n = 0; n < N; ++n) zb[n] += 2 * P;
-    }
-  } else {
-#pragma unroll 1
-    for (int e = 0; e < nv; ++e) {
-      load(0, 0);
-      add(0);
-      za += P;
-#pragma unroll
-      for (int n = 0; n < N; ++n) zb[n] += P;
-    }
+    for (int n = 0; n < N; ++n) zb[n] += P;
   }
 #pragma unroll
   for (int n = 0; n < N; ++n) {

@@ -6,7 +6,7 @@ namespace sbv {
 int n_variants() { return kNumVariants; }
 Variant variant(int v) { return Variant{kRow[v].ntm, kRow[v].nw}; }
 int waves_per_cu(int prec, int v) { return 4 * (prec == 0 ? kRow[v].occ64 : kRow[v].occ32); }
-int tile_slots(int prec, int v) { return prec == 0 && kRow[v].cap64 ? 256 * (4 * kRow[v].occ64 / kRow[v].nw) : 0; }
+int tile_slots(int prec, int v) { return prec == 0 && kRow[v].cap64 ? kUnits * (4 * kRow[v].occ64 / kRow[v].nw) : 0; }
 int variant_for(int nA) {
   for (int v = 0; v < kNumVariants; ++v)
     if (nA <= kRow[v].ntm * kTile) return v;

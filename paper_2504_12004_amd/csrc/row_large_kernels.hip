@@ -28,7 +28,7 @@ int large_ntm(int nA) {
 }
 int large_slots(int prec, bool adjoint) {
   const LargeVariant v = prec == 0 ? kBig64 : adjoint ? kBig32Adj : kBig32;
-  return 256 * (4 * v.occ / v.nw);
+  return kUnits * (4 * v.occ / v.nw);
 }
 
 template <typename T, RowMode MODE>

@@ -10,6 +10,7 @@ namespace sbv {
 
 // Tile edge of every block factorisation (the 16x16 MFMA output tile).
 constexpr int kTile = 16;
+constexpr int kUnits = 256;  // compute units of the device
 // Largest input dimension supported by the fused kernels.
 constexpr int kMaxDim = 20;
 
@@ -57,7 +58,7 @@ constexpr int64_t tile_elems(int ntm) { return (int64_t)256 * ntm * (ntm + 1) / 
 
 // Tile rows of a large block beyond kLargeNTM, or -1 when it is not one: it fits a
 // register variant, exceeds 512 points, or has fewer conditioning points than those
-// rows.
+// rows (a handle refuses such a block).
 inline int large_prefix(int nA, int mi) {
   const int nt = (nA + kTile - 1) / kTile;
   const int p = nt - kLargeNTM;
@@ -65,8 +66,9 @@ inline int large_prefix(int nA, int mi) {
   return p;
 }
 
-// Launchers (kernels.hip).  `count` is a device int; the kernel loops over
-// items[blockIdx.x + k*gridDim.x] while the index is below *count.
+// Launchers (row_kernels.hip, row_adjoint_kernels.hip, row_large_kernels.hip,
+// contract_kernels.hip, loglik_kernels.hip).  `count` is a device int; the kernel
+// loops over items[blockIdx.x + k*gridDim.x] while the index is below *count.
 // dmax is the largest input dimension among the sets (it sizes the LDS).  With
 // `queue` set, workgroups take their items from that device counter instead (one
 // atomic increment per item, starting at 0), so that one persistent launch can
@@ -123,12 +125,11 @@ void merge_small(std::vector<List>& per) {
     per[v].clear();
   }
 }
-hipError_t launch_reduce(const SetDesc* sets, int n_sets, const int* set_k, double* out, int* bad,
-                         hipStream_t s);
+hipError_t launch_reduce(const SetDesc* sets, int n_sets, double* out, int* bad, hipStream_t s);
 hipError_t launch_flag_compact(const SetDesc* sets, const WorkItem* items, const int* count,
                                WorkItem* out_items, int* out_count, hipStream_t s);
 hipError_t launch_zero_int(int* p, int n, hipStream_t s);
-int max_grid(int prec, int variant);
+int max_grid(int variant);  // workgroups of a launch whose number of blocks only the device knows
 
 }  // namespace sbv
 
