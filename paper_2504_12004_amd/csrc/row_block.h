@@ -46,9 +46,9 @@
 // do not overlap (an FP64 MFMA holds the vector pipe for its 64 cycles); half of a
 // wave's time is spent at the two barriers and behind LDS reads.  Measured per
 // evaluation, against the right-looking kernel with all tiles in registers and one
-// block per unit: n = 1e6, m = 200 17.2 -> 9.89 ms; n = 2e4, m = 60 152 -> 52 us; n =
-// 2e5, m = 200 in FP32 3.24 -> 1.4 ms; n = 1e5, m = 400 (a two-kernel path then) 12.6 ->
-// 5.32 ms; value and gradient n = 2e5, m = 200 10.6 -> 4.07 ms.
+// block per unit: n = 1e6, m = 200 17.3 -> 10.1 ms; n = 2e4, m = 60 153 -> 52 us; n =
+// 2e5, m = 200 in FP32 3.26 -> 1.45 ms; n = 1e5, m = 400 (a two-kernel path then) 12.7 ->
+// 5.45 ms; value and gradient n = 2e5, m = 200 10.6 -> 4.13 ms.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -382,7 +382,7 @@ __device__ __forceinline__ void gen_tiles(const double* z, const double* tab, in
 // was most of the error of the FP32 terms: without it the errors of value and
 // gradient against FP64 are 0.4 times those of covariances rounded to FP32 (n = 1e5, d =
 // 10, m = 200, tau^2 = 1e-3, sixteen datasets; emulated, 220 points, d = 5: 1.14e-3 of a
-// term's 1.22e-3).  The price, n = 2e5, m = 200: 1103 + 382 us instead of 873 + 285 us.
+// term's 1.22e-3).  The price, n = 2e5, m = 200: 1088 + 377 us instead of 873 + 285 us.
 template <typename T>
 __device__ __forceinline__ T low_part(double v) {
   return sizeof(T) == 8 ? T(0) : T(v - (double)T(v));
@@ -1069,7 +1069,8 @@ __global__ __launch_bounds__(NW * 64, OCC) void k_block_rows(const SetDesc* __re
 // instead of 2444 (cap 10: 2242, 12: 2167, 14: 2160, 16: 2155), the 14-tile ones 7820
 // instead of 8060 (cap 10: 8005, 12: 7909, 14: 7820, 16: 7880, 18: 8095).  With the
 // adjoint solves, n = 2e5: 16-tile variant 668 instead of 747 us, 14-tile 2270 instead
-// of 2160.  Three blocks per unit spill in every loop (14 tiles: 9250 us).
+// of 2160.  Three blocks per unit spill in every loop (14 tiles: 9250 us).  (Sweeps
+// made before the exponential underflowed to 0, which added up to 1 %.)
 struct RowVariant {
   int ntm, nw, occ64, occ32, adj32, cap64, capa64;
 };
