@@ -136,3 +136,30 @@ def test_simulation(sbv):
     B.free()
     assert _copies_equal(y[LEAD:].reshape(COPIES, -1))
     assert np.max(np.abs(y[:len(ref)] - ref)) <= 1e-9 * max(1.0, np.max(np.abs(ref)))
+
+
+def test_captured_before_the_memory_exists(sbv):
+    """A caller's capture of an FP64 value on a plan that has only served FP32 runs without
+    the memory for a part of the factor; its replays equal the eager value, also after
+    eager calls have allocated that memory."""
+    import torch
+    X, y, th, _ = _inputs(10, 1e-3)
+    B, _ = _handle(sbv, X, y)
+    thd = torch.tensor(th, device="cuda")
+    out, eager = (torch.zeros(1, dtype=torch.float64, device="cuda") for _ in range(2))
+    sbv.sbv_loglik_dev(B, thd, 5, out, prec=1, stream=torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        sbv.sbv_loglik_dev(B, thd, 5, out, stream=torch.cuda.current_stream())
+    got = []
+    for step in range(3):
+        thd.copy_(torch.tensor(th + 0.01 * step, device="cuda"))
+        g.replay()
+        torch.cuda.synchronize()
+        sbv.sbv_loglik_dev(B, thd, 5, eager, stream=torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        got.append((out.item(), eager.item()))
+    assert all(a == b and np.isfinite(a) for a, b in got) and len(set(got)) == 3, got
+    del g
+    B.free()
